@@ -305,17 +305,18 @@ void check_conv_bf16_variant(const Geometry& g, const ConvPlan& p, bool fused, R
             if (nitems > kConvThreads * p.fused_ipt || p.fused_ipt > kBf16FusedItems || (g.w & 1))
                 r.fail("%s tile %lld: %d raw items, registers hold %d", what, (long long)t, nitems,
                        kConvThreads * p.fused_ipt);
-            for (int q = 0; q < nitems && r.violations < 16; ++q) {
-                const int e0 = 2 * (q >> 1);
-                const int rr2 = e0 / (int)g.w, xx = e0 - rr2 * (int)g.w;
-                int sg = rr2 < rw.r0 ? 0 : 1 + (rr2 - rw.r0) / std::max(a.rmid, 1);
-                if (sg > tr.nseg - 1) sg = tr.nseg - 1;
-                const int yy = sg == 0 ? rw.ylo0 + rr2 : a.ylo_mid + (rr2 - rw.r0 - (sg - 1) * a.rmid);
-                if (yy < 0 || yy >= g.h || xx + 1 >= g.w + 1 || tr.i0 + sg >= g.n) {
+            // (every thread loads, the ones past the last item too: 256
+            // threads x fused_ipt, or 512 of the 128 x 256 tile)
+            const int slots = std::max(kConvThreads * p.fused_ipt, p.bn == 256 ? 2 * kConvThreads : 0);
+            for (int q = 0; q < slots && r.violations < 16; ++q) {
+                const RawItem it = raw_item(a, tr, rw, q);
+                const int sg = it.s, yy = it.yy, xx = it.xx;
+                if (yy < 0 || yy >= g.h || xx < 0 || xx + 1 >= g.w || sg < 0 || tr.i0 + sg >= g.n) {
                     r.fail("%s tile %lld: item %d reads x row %d col %d of image %d", what, (long long)t, q, yy,
                            xx, tr.i0 + sg);
                     break;
                 }
+                if (q >= nitems) continue;   // loaded, never expanded
                 const int m_st = tr.seg_m(sg), q_st = tr.seg_q(sg), len = tr.seg_len(sg);
                 const int m_end = sg == tr.nseg - 1 ? tr.m1 : (int)g.ho - 1;
                 for (int m = m_st; m <= m_end; ++m) {

@@ -793,26 +793,14 @@ __global__ __launch_bounds__(NT) void conv_bf16_fused_kernel(ConvArgs a) {
     const int64_t xplane = (int64_t)a.h * a.w_in;
     const int nitems = rr.rtot * a.w_in;   // (rtot*W/2 pairs) x 2 halves
 
-    // item q: half g = q & 1, element pair e0 = 2*(q >> 1) of the raw rows
-    // -> raw row r, column xx (even), segment s, input row yy
-    auto item_at = [&](int q, int* s, int* yy, int* xx) {
-        const int e0 = 2 * (q >> 1);
-        const int r = (int)fast_div((uint32_t)e0, a.div_w);
-        *xx = e0 - r * a.w_in;
-        *s = r < rr.r0 ? 0 : 1 + (int)fast_div((uint32_t)(r - rr.r0), a.div_rmid);
-        if (*s > tr.nseg - 1) *s = tr.nseg - 1;
-        *yy = *s == 0 ? rr.ylo0 + r : a.ylo_mid + (r - rr.r0 - (*s - 1) * a.rmid);
-    };
-    // item sources: channel 0 of the thread's items (items past nitems load
-    // item q & 1 instead, a valid address, and are never expanded)
+    // item sources: channel 0 of the thread's items (items past nitems load a
+    // valid address too, and are never expanded)
     int64_t xbase[IPT];
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
-        int q = threadIdx.x + j * NT;
-        if (q >= nitems) q &= 1;
-        int sg, yy, xx;
-        item_at(q, &sg, &yy, &xx);
-        xbase[j] = ((int64_t)(tr.i0 + sg) * a.c + 8 * (q & 1)) * xplane + (int64_t)yy * a.w_in + xx;
+        const int q = threadIdx.x + j * NT;
+        const RawItem it = raw_item(a, tr, rr, q);
+        xbase[j] = ((int64_t)(tr.i0 + it.s) * a.c + 8 * (q & 1)) * xplane + (int64_t)it.yy * a.w_in + it.xx;
     }
     // expansion map of this thread's items
     FusedMap<FH> mp[IPT];
@@ -824,8 +812,8 @@ __global__ __launch_bounds__(NT) void conv_bf16_fused_kernel(ConvArgs a) {
 #pragma unroll
         for (int i = 0; i < FH; ++i) mp[j].dst[0][i] = mp[j].dst[1][i] = spare;
         if (q < nitems) {
-            int sg, yy, xx;
-            item_at(q, &sg, &yy, &xx);
+            const RawItem it = raw_item(a, tr, rr, q);
+            const int sg = it.s, yy = it.yy, xx = it.xx;
             const int m_st = sg == 0 ? tr.m0 : 0, q_st = sg == 0 ? tr.qa0 : 0;
             const int len = sg == 0 ? tr.len0 : (sg == tr.nseg - 1 ? tr.len_last : tr.len_mid);
             const int m_end = sg == tr.nseg - 1 ? tr.m1 : a.ho - 1;

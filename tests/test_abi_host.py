@@ -183,6 +183,34 @@ def test_launch_plans_in_bounds_on_paper_layers():
                 assert P.im2win_check_plan(d) == 0, (layer["name"], P.im2win_last_error())
 
 
+# Padding taller than the filter: some pixel tiles read padding alone and have
+# no input row to stage (n, c, h, w, k, fh, fw, sh, sw, ph, pw).  In bf16 they
+# cover every tile of the fused kernel that stages pairs of input elements:
+# 64 x 64, 64 x 128, 128 x 128 and 128 x 256.
+PADDING_TILES = [
+    (1, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),
+    (2, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),      # tiles over two images, in the padding of both
+    (1, 16, 8, 8, 64, 3, 3, 1, 1, 2000, 1),
+    (1, 32, 4, 64, 64, 1, 1, 1, 1, 1, 0),      # 1x1 with padding 1: its outer rows see padding alone
+    (1, 16, 9, 12, 64, 3, 5, 2, 2, 40, 2),
+    (60, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),
+    (8, 16, 8, 64, 128, 3, 3, 1, 1, 32, 1),
+    (60, 16, 8, 8, 128, 3, 3, 1, 1, 32, 1),
+]
+
+
+@pytest.mark.parametrize("layout", [0, 1], ids=["padded", "trimmed"])
+@pytest.mark.parametrize("dtype", [P.IM2WIN_F32, P.IM2WIN_BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", PADDING_TILES, ids=lambda c: "x".join(map(str, c)))
+def test_launch_plans_in_bounds_on_tiles_of_padding_alone(case, dtype, layout):
+    """Every thread's loads stay inside x, those of threads without an item
+    of the tile too."""
+    d = P.im2win_desc(*case, dtype, layout)
+    if dtype == P.IM2WIN_BF16:
+        assert P.im2win_conv_kernel(d, True) == "bf16_tiles"
+    assert P.im2win_check_plan(d) == 0, P.im2win_last_error()
+
+
 # Shapes that the fp32 band kernel takes (n, c, h, w, k, fh, fw, sh, sw, ph,
 # pw): C a multiple of 16, K of 32 (64 with the two-way reduction split), a
 # band of output rows of 97-224 pixels (four-way split) or 353-416 (two-way),

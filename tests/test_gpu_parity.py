@@ -201,6 +201,34 @@ def test_edge_shapes(case, dtype):
     assert np.array_equal(y_unf, y_fus), "fused and unfused outputs differ"
 
 
+# Padding taller than the filter: some pixel tiles read padding alone and have
+# no input row to stage (bf16: every tile of the fused kernel that stages
+# pairs of input elements).
+PADDING_TILES = [
+    (1, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),      # 64 x 64 tiles
+    (2, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),      # tiles over two images, in the padding of both
+    (1, 32, 4, 64, 64, 1, 1, 1, 1, 1, 0),      # 1x1 with padding 1: its outer rows see padding alone
+    (1, 16, 9, 12, 64, 3, 5, 2, 2, 40, 2),
+    (60, 16, 8, 8, 64, 3, 3, 1, 1, 32, 1),     # 64 x 128 tiles
+    (8, 16, 8, 64, 128, 3, 3, 1, 1, 32, 1),    # 128 x 128 tiles
+    (60, 16, 8, 8, 128, 3, 3, 1, 1, 32, 1),    # 128 x 256 tiles
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", PADDING_TILES, ids=lambda c: "x".join(map(str, c)))
+def test_tiles_of_padding_alone(case, dtype):
+    n, c, h, w, k, fh, fw, sh, sw, ph, pw = case
+    wl, x_cpu, w_cpu = workloads.random_case(sum(case), n, c, h, w, k, fh, fw, sh, sw, ph, pw, dtype)
+    _label("padding-tiles", wl)
+    assert P.im2win_check_plan(_desc(wl)) == 0, P.im2win_last_error()
+    ref, ref_abs = oracle.direct_conv(_shape(wl), _f64(x_cpu), _f64(w_cpu), with_abs=True)
+    y_unf = _run_conv(wl, x_cpu, w_cpu, n, False)
+    y_fus = _run_conv(wl, x_cpu, w_cpu, n, True)
+    _assert_close(y_fus, ref, ref_abs, c * fh * fw, dtype, "fused")
+    assert np.array_equal(y_unf, y_fus), "fused and unfused outputs differ"
+
+
 # Shapes that the fp32 band kernel takes (at least 85% of whole rounds of 256
 # workgroups useful), each in both row layouts; the copy granularity (16-byte
 # or 4-byte pieces of the strips) follows from the plane alignment.
