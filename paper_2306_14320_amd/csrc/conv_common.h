@@ -188,22 +188,22 @@ __host__ __device__ inline RawRows raw_rows(const TileRuns& tr, const ConvArgs& 
 // channels of half q & 1.  Items count the element pairs of the tile's raw
 // rows, rtot*W/2 pairs x 2 halves (W is even).  A thread past the last item
 // repeats the first one of its half; a tile that lies in the padding alone
-// has no raw row to repeat, so its threads take row 0 of its first image
-// (loaded, never expanded).
+// has no raw row to repeat, and below the input its threads take the last
+// row (loaded, never expanded).
 struct RawItem {
     int s, yy, xx;
 };
 
 __host__ __device__ inline RawItem raw_item(const ConvArgs& a, const TileRuns& tr, const RawRows& rr, int q) {
-    RawItem it{0, 0, 0};
-    if (rr.rtot == 0) return it;
+    RawItem it;
     if (q >= rr.rtot * a.w_in) q &= 1;
     const int e0 = 2 * (q >> 1);
     const int r = (int)fast_div((uint32_t)e0, a.div_w);
     it.xx = e0 - r * a.w_in;
     it.s = r < rr.r0 ? 0 : 1 + (int)fast_div((uint32_t)(r - rr.r0), a.div_rmid);
     if (it.s > tr.nseg - 1) it.s = tr.nseg - 1;
-    it.yy = it.s == 0 ? rr.ylo0 + r : a.ylo_mid + (r - rr.r0 - (it.s - 1) * a.rmid);
+    const int yy = it.s == 0 ? rr.ylo0 + r : a.ylo_mid + (r - rr.r0 - (it.s - 1) * a.rmid);
+    it.yy = yy < a.h ? yy : a.h - 1;
     return it;
 }
 
