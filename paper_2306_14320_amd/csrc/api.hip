@@ -11,6 +11,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "conv_common.h"
 #include "direct.h"
 
 // Filter scratch of im2win_conv2d_fused_noalloc: a static device array, so
@@ -351,6 +352,14 @@ int im2win_selftest(void) {
             }
         }
     }
+    // the channel planes of a window tensor whose plane is near 2^31 elements
+    im2win::ConvArgs a{};
+    a.ho = 310000;
+    for (int row_len : {1000, 6927})
+        for (int ch = 0; ch < 16; ++ch) {
+            a.row_len = row_len;
+            if (im2win::ws_channel_offset(a, ch) != int64_t(ch) * 310000 * row_len) ++failures;
+        }
     return failures;
 }
 

@@ -596,7 +596,7 @@ __global__ __launch_bounds__(NT) void conv_bf16_fast_kernel(ConvArgs a) {
 
     // per-item sources (channel 0 of the chunk) and LDS destinations
     const uint16_t* src = static_cast<const uint16_t*>(a.src);
-    const int plane = a.ho * a.row_len;
+    const int64_t plane = ws_channel_offset(a, 1);
     const uint16_t* sp[SVI];
     int sdst[SVI];
     const int nitems = 2 * rn.ck_total;
@@ -632,10 +632,10 @@ __global__ __launch_bounds__(NT) void conv_bf16_fast_kernel(ConvArgs a) {
         const int r0 = chc * kRC;
 #pragma unroll
         for (int k = 0; k < SVI; ++k) {
-            const uint16_t* p = sp[k] + (int64_t)r0 * plane;
+            const uint16_t* p = sp[k] + ws_channel_offset(a, r0);
 #pragma unroll
             for (int c8 = 0; c8 < 8; ++c8) {
-                const u32x2 v = load8(p + c8 * plane);
+                const u32x2 v = load8(p + ws_channel_offset(a, c8));
                 r.sd[k][2 * c8] = v[0];
                 r.sd[k][2 * c8 + 1] = v[1];
             }

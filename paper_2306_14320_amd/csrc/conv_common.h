@@ -59,6 +59,12 @@ struct ConvArgs {
 };
 
 
+// Window-tensor elements from a channel's plane to the plane `ch` channels on
+// (64-bit: one plane holds up to 2^31 - 1 elements).
+__host__ __device__ inline int64_t ws_channel_offset(const ConvArgs& a, int ch) {
+    return (int64_t)ch * a.ho * a.row_len;
+}
+
 // Geometry of the window-tensor runs that one pixel tile reads (per channel).
 struct TileRuns {
     int p0, plast;

@@ -458,5 +458,31 @@ def test_shapes_without_an_lds_tile(case, dtype):
     _assert_close(y_fus, ref, ref_abs, nterms, dtype, "fused")
 
 
+def test_bf16_channel_planes_past_2_to_31_elements():
+    """A tall bf16 layer whose channel planes are 310M elements each, so that
+    the eighth channel of a staging item lies past 2^31 elements: 1x1, stride
+    9 across, from a window tensor of 9.9 GB, on rows at both ends and in the
+    middle against the product in fp32."""
+    d = P.im2win_desc(1, 16, 310000, 1000, 64, 1, 1, 1, 9, 0, 0, P.IM2WIN_BF16)
+    assert P.im2win_conv_kernel(d, False) == "bf16_tiles"
+    assert P.im2win_filter_scratch_bytes(d) == 64 * 16 * 2   # the kernel with the packed filter
+    print("[parity] tall channel planes", flush=True)
+    ho, wo = P.im2win_output_shape(d)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    ws = torch.empty(P.workspace_shape(d), dtype=torch.bfloat16, device=DEV)
+    for r in range(16):
+        ws[0, r].uniform_(-1, 1, generator=g)
+    w = torch.randn(64, 16, 1, 1, generator=g, device=DEV).to(torch.bfloat16)
+    y = P.conv2d(ws, w, d)
+    torch.cuda.synchronize()
+    for m in (0, ho // 2, ho - 500):
+        cols = ws[0, :, m:m + 500, :9 * wo:9].double().reshape(16, -1)
+        wm = w.double().reshape(64, 16)
+        ref, ref_abs = wm @ cols, wm.abs() @ cols.abs()
+        got = y[0, :, m:m + 500].reshape(64, -1).double()
+        _assert_close(got.cpu().numpy(), ref.cpu().numpy(), ref_abs.cpu().numpy(), 16, "bf16", f"rows from {m}")
+
+
 def test_one_hip_runtime_after_gpu_use():
     assert len(P.hip_runtimes_mapped()) == 1, P.hip_runtimes_mapped()
