@@ -69,7 +69,8 @@ __device__ inline void zero_channels(float* S, const ConvArgs& a, const TileRuns
 //   F[jj][0 .. rc_act*T)   filter rows in natural (r, u, v) order
 //   S[rc][0 .. strip_len)  window-tensor runs (unfused), or the same strip
 //                          positions gathered from x, zero where they fall in
-//                          the padding (fused)
+//                          the padding (fused bf16; fused fp32 stages the
+//                          input rows instead, stage_raw)
 template <typename TIn, bool FUSED, bool FILTER_ONLY = false>
 __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRuns& tr, int j0,
                              int r0, int rc_act, int rc_stage) {
@@ -78,6 +79,7 @@ __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRu
     const int kreal = rc_act * a.taps;
     const int nrows_f = min(a.k - j0, a.bm);
     constexpr bool kDma = sizeof(TIn) == 4;
+    // (fp32 plans read the filter repacked or in whole 16-byte vectors)
     if (kDma && a.fpack) {
         // the repacked filter holds this tile's chunk as one block laid out
         // like the LDS rows (zeros past the chunk's taps and past K): 16-byte
@@ -90,7 +92,7 @@ __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRu
             const int c = c0 + lane;
             if (c < units) __builtin_amdgcn_global_load_lds(blk + 4 * c, (lds_void*)(F + 4 * c0), 16, 0, 0);
         }
-    } else if (kDma && a.fvec) {
+    } else if (kDma) {
         // filter rows are whole 16-byte chunks (C*T and the chunk's rc*T are
         // multiples of 4): one DMA instruction fills 64 consecutive 16-byte
         // chunks of the row-major tile (rows of stride fp, a multiple of 4)
@@ -104,19 +106,6 @@ __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRu
             const int col = c - jj * cpr;
             if (c < total && col < creal)
                 __builtin_amdgcn_global_load_lds(w + jj * wrow + 4 * col, (lds_void*)(F + 4 * c0), 16, 0, 0);
-        }
-    } else if (kDma) {
-        // one DMA instruction fills 64 consecutive LDS floats of the row-major
-        // tile (rows of stride fp), lane by lane from the matching filter row
-        const float* w = static_cast<const float*>(a.w) + ((int64_t)j0 * a.c + r0) * a.taps;
-        const int64_t wrow = (int64_t)a.c * a.taps;
-        const int total = nrows_f * a.fp;
-        for (int e0 = wave * 64; e0 < total; e0 += (int)blockDim.x) {
-            const int e = e0 + lane;
-            const int jj = (int)fast_div((uint32_t)e, a.div_fp);
-            const int col = e - jj * a.fp;
-            if (e < total && col < kreal)
-                __builtin_amdgcn_global_load_lds(w + jj * wrow + col, (lds_void*)(F + e0), 4, 0, 0);
         }
     } else {
         const TIn* w = static_cast<const TIn*>(a.w);
@@ -220,10 +209,6 @@ __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRu
                 if (e < len) {
                     if (!inb)
                         l[e] = 0.0f;
-                    else if (kDma)
-                        __builtin_amdgcn_global_load_lds(
-                            reinterpret_cast<const float*>(plane) + (int64_t)yy * a.w_in + xx,
-                            (lds_void*)(l + e0), 4, 0, 0);
                     else
                         l[e] = to_f32(plane[(int64_t)yy * a.w_in + xx]);
                 }
