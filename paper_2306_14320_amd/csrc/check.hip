@@ -401,8 +401,8 @@ void check_conv_bf16_variant(const Geometry& g, const ConvPlan& p, bool fused, R
 }
 
 // Packed bf16 filter: every piece reads 8 channels inside w, the blocks tile
-// the packed buffer, and within a block the DMA destination of piece P (the
-// kernels' dma_filter: plane P / (T*BM), position P mod T*BM) is the LDS
+// the packed buffer, and within a block the LDS destination of piece P (the
+// kernels' fdst: plane P / (T*BM), position P mod T*BM) is the LDS
 // position packed_piece() assigns, where the matrix-core reads expect
 // channels c0 .. c0+7 of tap t of output channel j: each filter position of
 // both planes filled exactly once.
@@ -434,15 +434,15 @@ void check_packed_filter(const Geometry& g, const ConvPlan& p, Report& r) {
         const int jt = (int)(blk / nchunks), ch = (int)(blk % nchunks);
         const int gg = P / plane, q = P % plane, t = q / bm, jj = q % bm;
         const int v = t / (int)g.fh, u = t % (int)g.fh;
-        const int dma_pos = gg * (int)p.cl_fpb + P - gg * plane;
+        const int st_pos = gg * (int)p.cl_fpb + P - gg * plane;
         if (pc.j != jt * bm + jj || pc.j >= g.k || pc.c0 != 16 * ch + 8 * gg || pc.c0 + 8 > g.c ||
             packed_index(pc.j, ch, gg, t, T, bm, nchunks) != gid || g.k % kPackRows ||
-            pc.nat != u * g.fw + v || pc.nat >= T || pc.lds_pos != dma_pos || dma_pos < 0 ||
-            dma_pos >= 2 * p.cl_fpb || (gg == 0 && dma_pos >= p.cl_fpb))
-            r.fail("conv: packed filter piece %lld -> j %d c0 %d tap %d LDS %d (DMA %d)", (long long)gid, pc.j,
-                   pc.c0, pc.nat, pc.lds_pos, dma_pos);
+            pc.nat != u * g.fw + v || pc.nat >= T || pc.lds_pos != st_pos || st_pos < 0 ||
+            st_pos >= 2 * p.cl_fpb || (gg == 0 && st_pos >= p.cl_fpb))
+            r.fail("conv: packed filter piece %lld -> j %d c0 %d tap %d LDS %d (stored at %d)", (long long)gid, pc.j,
+                   pc.c0, pc.nat, pc.lds_pos, st_pos);
         else if (blk == 0)
-            ++seen[dma_pos];
+            ++seen[st_pos];
     }
     for (int gg = 0; gg < 2 && r.violations < 16; ++gg)
         for (int q = 0; q < plane; ++q)

@@ -274,7 +274,7 @@ __host__ __device__ inline int cl_pixel_base(const ClLayout& c, const TileRuns& 
 // laid out as the filter planes of an LDS stage: piece P = g*T*BM + t*BM + jj
 // holds channels 16ch + 8g .. 16ch + 8g + 7 of tap t (window order
 // t = v*Fh + u) of output channel jt*BM + jj.  A chunk's block is therefore
-// one contiguous range that 16-byte DMA copies into LDS unchanged.
+// one contiguous range whose 16-byte pieces go to LDS unchanged.
 struct PackedPiece {
     int j, c0, nat, lds_pos;   // output channel, first input channel, tap (u*Fw + v), LDS position
 };
@@ -627,9 +627,10 @@ int launch_conv_f32_band(const Geometry& g, const F32BandPlan& p, bool fused, co
 // The band kernel for layers with few input channels (conv_f32_band.hip):
 // all C channels' strips of a band in LDS at once (one slot of slotf floats
 // per channel, two buffers), 64 output channels per workgroup, the two
-// k-slots of an MFMA holding the top and the bottom half of the filter rows,
-// two waves per block of 32 output channels splitting the k-steps; one
-// persistent workgroup per CU walks through per_wg consecutive bands.
+// k-slots of an MFMA holding two channels, or the top and the bottom half of
+// the last channel's filter rows (smallc_step), two waves per block of 32
+// output channels splitting the k-steps; one persistent workgroup per CU walks
+// through per_wg consecutive bands.
 constexpr int kSmallCChannels = 3;          // C the kernels are built for
 constexpr int kSmallCWavesPerSimd = 2;      // 8 waves, each half of the band's pixel blocks
 
@@ -666,6 +667,12 @@ struct SmallCStep {
 __host__ __device__ constexpr int smallc_steps(int c, int fh, int fw) {
     return (c / 2) * fh * fw + (c % 2) * ((fh + 1) / 2) * fw;
 }
+// The k-steps per band that the plan's line counts: row halves for every
+// channel, 198, 84 and 18 for three channels of 11x11, 7x7 and 3x3 filters
+// where the kernel runs smallc_steps = 187, 77 and 15.  The margin keeps
+// layers on the tiles that are faster there (plan_band_small_c_f32 says what
+// both sides measured).
+constexpr int smallc_gate_steps(int c, int fh, int fw) { return c * ((fh + 1) / 2) * fw; }
 __host__ __device__ constexpr SmallCStep smallc_step(int c, int fh, int fw, int q, int slot) {
     const int ga = (c / 2) * fh * fw;
     if (q < ga) {
@@ -707,8 +714,9 @@ __host__ __device__ inline int smallc_parts(const F32BandArgs& a, const BandTile
 // 11x11 filter; K a multiple of 32, in groups of 64; a band of rows whose
 // pixels fill 4-7 blocks of 32 and whose three strips (or raw input rows),
 // twice, fit with the partial sums in LDS; at least 55% of the occupied
-// matrix-core work useful, counting ceil(bands / 256) bands per workgroup
-// and the idle half of a last group of 32 channels).  Independent of fusion.
+// matrix-core work useful, counting smallc_gate_steps per band,
+// ceil(bands / 256) bands per workgroup and the idle half of a last group of
+// 32 channels).  Independent of fusion.
 F32BandPlan plan_band_small_c_f32(const Geometry& g);
 F32BandArgs band_args_small_c_f32(const Geometry& g, const F32BandPlan& p, bool fused, const void* src,
                                   const void* w, float* y);
@@ -774,8 +782,6 @@ __host__ __device__ inline RawRowEntry raw_row_entry(const ConvArgs& a, const Ti
     return e;
 }
 
-// Upper bound of RawRows::rtot over all tiles of `bn` pixels: the window
-// rows a tile spans, each segment adding the filter height.
 // Upper bound of RawRows::rtot over all tiles of `bn` pixels.  A segment of
 // q window rows uses (q - 1)*sh + Fh input rows, and at most H; a tile spans
 // at most dmax + 1 window rows in ns segments, so at most

@@ -16,8 +16,10 @@
 //   - unfused: the runs and the filter rows are copied straight from global
 //     memory into LDS by the global_load_lds DMA path (no register round
 //     trip; a wave issues every copy of the chunk, then waits once);
-//   - fused: the strips are built in LDS from x, zero padding included
-//     (gathers batched eight per thread), the window tensor is never written;
+//   - fused: the strips are built in LDS from x, zero padding included (fp32:
+//     the chunk's input rows are copied to LDS and expanded into the strips
+//     there; bf16 widened: gathered element by element), the window tensor is
+//     never written;
 //   - v_mfma_f32_32x32x2f32 runs with A = filter rows (32 channels) and
 //     B = window columns (32 pixels); each accumulator register then holds 32
 //     consecutive pixels of one output channel, so NCHW stores coalesce.
@@ -164,7 +166,7 @@ __device__ inline void stage(float* S, float* F, const ConvArgs& a, const TileRu
     if (!FUSED && kDma && nruns < nw) {
         // fewer runs than waves (one or two channels): blocks of 64 floats of
         // the runs, counted run after run, to the waves round-robin (block gb
-        // goes to wave gb % 4); otherwise whole runs, below
+        // goes to wave gb % nw); otherwise whole runs, below
         const float* srcf = reinterpret_cast<const float*>(src);
         int gstart = 0;   // blocks before the current run
         for (int rc = 0; rc < rc_act; ++rc)
@@ -241,8 +243,8 @@ __device__ inline int raw_segment(int r, const RawRows& rr, int nseg, const Conv
 // floats) of all the chunk's channels, in blocks of 64, go to the waves
 // round-robin (raw_blocks); expand_raw uses the same assignment, so a wave
 // expands what it copied, and chunks of fewer than four channels keep every
-// wave busy.  Otherwise wave w copies channels w, w + 4, ... (the expansion
-// map reads raw rows only after a barrier).
+// wave busy.  Otherwise wave w copies channels w, w + nw, ... of the nw waves
+// (the expansion map reads raw rows only after a barrier).
 __device__ inline int raw_blocks(const ConvArgs& a, const RawRows& rr, int* units) {
     *units = a.xvec ? (rr.rtot * a.w_in) >> 2 : rr.rtot * a.w_in;
     return (*units + 63) >> 6;
@@ -276,7 +278,7 @@ __device__ inline void stage_raw(float* X, const ConvArgs& a, const TileRuns& tr
         }
     };
     if constexpr (BLOCKS) {
-        // block rc*nb + b goes to wave (rc*nb + b) % 4
+        // block rc*nb + b goes to wave (rc*nb + b) % nw
         for (int rc = 0; rc < rc_act; ++rc)
             for (int b = (wave - rc * nb) & (nw - 1); b < nb; b += nw) copy_block(rc, b * 64);
     } else {

@@ -417,15 +417,16 @@ __global__ __launch_bounds__(2 * kBandThreads, 1) void conv_f32_band8_kernel(F32
 // is input row m*sh + u, column n*sw + v - pw, a fixed offset from the
 // window's start, as in the window tensor.  The filter values stay in
 // registers across the run; they are reloaded only where the run crosses
-// into the next group of output channels.  The MFMA's two k-slots take
-// filter rows u and u + Fh - ceil(Fh/2) of one channel and tap column (one
-// LDS read: the second slot is the first plus Fh - ceil(Fh/2) rows),
-// u < ceil(Fh/2); for odd Fh the middle row comes up in both slots and the
-// second slot's copy gets zero weights, so every read stays inside the
-// pixel's window.  Waves (cb, ks): 2 blocks of 32 output channels x 2
-// halves of the C*ceil(Fh/2)*Fw k-steps; with WPS = 2 waves w and w + 4 take
-// wave w's share for the first ceil(NB/2) pixel blocks and the rest, two
-// waves per SIMD, and the staging copies go round the 8 waves.
+// into the next group of output channels.  The MFMA's two k-slots take, at
+// one filter tap, the two channels of a pair, and for the last channel filter
+// rows u and u + Fh - ceil(Fh/2), u < ceil(Fh/2), at one tap column; either
+// way the second slot is the first plus a constant, so one LDS read per step
+// serves both (smallc_step).  For odd Fh the last channel's middle row comes
+// up in both slots and the second slot's copy gets zero weights, so every
+// read stays inside the pixel's window.  Waves (cb, ks): 2 blocks of 32
+// output channels x 2 halves of the smallc_steps k-steps; with WPS = 2 waves
+// w and w + 4 take wave w's share for the first ceil(NB/2) pixel blocks and
+// the rest, two waves per SIMD, and the staging copies go round the 8 waves.
 template <int C, int FH, int FW, int NB, int MODE, int WPS>
 __global__ __launch_bounds__(WPS * kBandThreads, 1) void conv_f32_band_small_c_kernel(F32BandArgs a) {
     constexpr int HU = (FH + 1) / 2;
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(WPS * kBandThreads, 1) void conv_f32_band_small_c_k
 
     // Unfused: the C strips of band bid (runs of the window tensor) into
     // strip buffer buf, parts of 256 (wide) or 64 elements; copy c*np + sp
-    // goes to wave (c*np + sp) mod 4.  Copies past the strip read zeros.
+    // goes to wave (c*np + sp) mod NWV.  Copies past the strip read zeros.
     auto issue_strips = [&](int bid, int buf) {
         const BandTile t = smallc_tile(a, bid);
         const __amdgpu_buffer_rsrc_t sres = band_rsrc(a.src + (size_t)t.img * img_elems, (uint32_t)(img_elems * 4));
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(WPS * kBandThreads, 1) void conv_f32_band_small_c_k
     // outside the image) of the C channels into raw buffer buf, columns
     // 0..W-1 at rlpad, in rparts copies per row (16-byte pieces, or 4-byte
     // ones when rows are not whole vectors); row c*rrows + r goes to wave
-    // (c*rrows + r) mod 4.  The pad columns around them were zeroed once and
+    // (c*rrows + r) mod NWV.  The pad columns around them were zeroed once and
     // are never written.  With them the raw rows hold every window element
     // of the band at a fixed offset from the window's start, so the k-steps
     // read them as they read the window tensor's strips.
@@ -1004,9 +1005,10 @@ F32BandPlan plan_band_small_c_f32(const Geometry& g) {
     if (g.c * g.h * g.w * 4 >= (int64_t(1) << 30) || g.c * g.ho * g.row_len * 4 >= (int64_t(1) << 30) ||
         g.k * g.c * g.taps * 4 >= (int64_t(1) << 31) || g.k * g.ho * g.wo * 4 >= (int64_t(1) << 30))
         return best;
-    const int HU = (int)(g.fh + 1) / 2, S = kSmallCChannels * HU * (int)g.fw, SW = (S + 1) / 2;
-    // useful MFMA k-steps (pairs of reduction elements) over those the launch
-    // occupies: whole workgroups per CU, each 4 waves of NB blocks x SW steps
+    const int S = smallc_gate_steps(kSmallCChannels, (int)g.fh, (int)g.fw), SW = (S + 1) / 2;
+    // useful MFMA k-steps (pairs of reduction elements) over those a launch
+    // with S k-steps per band occupies: whole workgroups per CU, each 4 waves
+    // of NB blocks x SW steps
     const double useful = (double)g.n * (g.k / 32) * (double)(g.ho * g.wo) / 32.0 * (g.c * g.taps / 2.0);
     for (int64_t rows = 1; rows <= g.ho; ++rows) {
         const int64_t nb = (rows * g.wo + 31) / 32;
@@ -1030,6 +1032,13 @@ F32BandPlan plan_band_small_c_f32(const Geometry& g) {
             best.lds_bytes = lds;
         }
     }
+    // Below the line the tiles run.  Counted in the k-steps that the kernel
+    // runs it lies at 62% (3x3), 59% (7x7) and 58% (11x11).  A line at 57.5%
+    // of those would add layers of two kinds (90 timed).  Where a workgroup
+    // walks three or more bands this kernel is 0.78x to 1.37x as fast as the
+    // tiles for conv2d, slower on 8 layers of 40, and 0.96x to 1.88x fused.
+    // Where it walks one or two it is faster on all 50, 1.10x to 1.82x and
+    // 1.05x to 3.4x: a line of its own for short runs would pay.
     if (best.eff < 0.55) return F32BandPlan();
     best.ok = true;
     return best;

@@ -248,9 +248,9 @@ F32_BANDS = [
 ]
 
 
-# Shapes that the fp32 small-C band kernel takes: C = 3, 7x7 filters, K a
-# multiple of 64, bands of 97-224 pixels, at least 75% of the occupied
-# matrix-core work useful.
+# Shapes that the fp32 small-C band kernel takes: C = 3, 3x3, 7x7 or 11x11
+# filters, K a multiple of 32, bands of 97-224 pixels, at least 55% of the
+# occupied matrix-core work useful (row halves of every channel counted).
 F32_BANDS_SMALL_C = [
     (32, 3, 224, 224, 64, 7, 7, 2, 2, 3, 3),    # the stem layer: bands of 2 rows
     (128, 3, 227, 227, 64, 7, 7, 2, 2, 0, 0),   # Table 1 Conv3
@@ -277,6 +277,41 @@ def test_launch_plans_in_bounds_fp32_bands_small_c(case, layout):
     assert P.im2win_conv_kernel(d, False) == P.im2win_conv_kernel(d, True) == "f32_bands_small_c"
     assert P.im2win_filter_scratch_bytes(d) == 0
     assert P.im2win_check_plan(d) == 0, P.im2win_last_error()
+
+
+@pytest.mark.parametrize("case,taken", [
+    ((8, 3, 41, 41, 224, 3, 3, 1, 1, 0, 0), True),
+    ((18, 3, 44, 44, 192, 3, 3, 2, 2, 0, 0), False),
+    ((9, 3, 54, 54, 96, 7, 7, 1, 1, 0, 0), True),
+    ((15, 3, 73, 73, 64, 7, 7, 2, 2, 3, 3), False),
+    ((2, 3, 160, 160, 128, 7, 7, 2, 2, 3, 3), False),
+    ((20, 3, 80, 80, 160, 11, 11, 4, 4, 5, 5), True),
+    ((17, 3, 76, 76, 256, 11, 11, 4, 4, 5, 5), False),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_fp32_small_c_line_counts_row_halves(case, taken):
+    """Layers just above and just below the small-C kernel's line, 55% of the
+    occupied work useful with row halves counted for every channel; with the
+    k-steps that the kernel runs all of them would lie above it."""
+    n, c, h, w, k, fh, fw, sh, sw, ph, pw = case
+    ho, wo = (h + 2 * ph - fh) // sh + 1, (w + 2 * pw - fw) // sw + 1
+
+    def share(steps):
+        best = 0.0
+        for rows in range(1, ho + 1):
+            nb = -(-rows * wo // 32)
+            if 4 <= nb <= 7:   # (short rows: every such band fits in LDS)
+                per_wg = -(-n * -(-ho // rows) * -(-k // 64) // 256)
+                useful = n * (k / 32) * ho * wo / 32 * (c * fh * fw / 2)
+                best = max(best, useful / (per_wg * 256 * 4 * nb * -(-steps // 2)))
+        return best
+
+    row_halves = c * ((fh + 1) // 2) * fw
+    run = fh * fw + (fh + 1) // 2 * fw   # a channel pair, then the last channel's row halves
+    assert 0.54 < share(row_halves) < 0.56 and (share(row_halves) >= 0.55) == taken
+    assert share(run) >= 0.55
+    d = P.im2win_desc(*case, P.IM2WIN_F32)
+    want = "f32_bands_small_c" if taken else "f32_tiles"
+    assert P.im2win_conv_kernel(d, False) == P.im2win_conv_kernel(d, True) == want
 
 
 def test_conv_kernel_names_on_workloads():
