@@ -239,9 +239,9 @@ const char* im2win_last_error(void);
 
 /*
  * Host-side self check of the library's integer arithmetic helpers (division
- * by invariant divisors used for index decomposition, 64-bit channel offsets).
- * Returns 0 when every check passes, otherwise the number of failures.  No HIP
- * calls.
+ * by invariant divisors used for index decomposition, 64-bit channel offsets,
+ * the pixels of a tile near 2^31).  Returns 0 when every check passes,
+ * otherwise the number of failures.  No HIP calls.
  */
 int im2win_selftest(void);
 

@@ -352,6 +352,27 @@ int im2win_selftest(void) {
             }
         }
     }
+    // the last pixel tile of a layer of 2^31 - 2 output pixels: pixels past it
+    // are past 2^31 too
+    im2win::Geometry g{};
+    g.n = g.c = g.k = g.fh = g.fw = g.sh = g.sw = g.taps = 1;
+    g.h = g.ho = 42966;
+    g.w = g.wo = g.wp = g.row_len = g.used_len = 49981;
+    g.npix = g.ho * g.wo;
+    g.elem = 4;
+    const im2win::ConvArgs ta = im2win::make_conv_args(g, nullptr, nullptr, nullptr, 64);
+    for (int bn : {64, 128, 256}) {
+        const int64_t last = (g.npix - 1) / bn;
+        im2win::TileRuns tr;
+        tr.init((int)last, bn, ta);
+        if (tr.p0 != last * bn || tr.plast != g.npix - 1 || tr.nseg != 1) ++failures;
+        for (int off = 0; off < bn; ++off) {
+            bool valid;
+            const int p = im2win::tile_pixel(tr, off, &valid);
+            const bool want = last * bn + off < g.npix;
+            if (valid != want || p != last * bn + (want ? off : 0)) ++failures;
+        }
+    }
     // the channel planes of a window tensor whose plane is near 2^31 elements
     im2win::ConvArgs a{};
     a.ho = 310000;

@@ -231,9 +231,8 @@ void check_conv_variant(const Geometry& g, const ConvPlan& p, bool fused, Report
             }
         }
         for (int q = 0; q < p.bn; ++q) {
-            int px = tr.p0 + q;
-            const bool valid = px <= tr.plast;
-            if (!valid) px = tr.p0;
+            bool valid;
+            const int px = tile_pixel(tr, q, &valid);
             int64_t yoff;
             const int base = pixel_base(tr, a, px, &yoff);
             // the window must lie inside its own run of the strip
@@ -366,9 +365,8 @@ void check_conv_bf16_variant(const Geometry& g, const ConvPlan& p, bool fused, R
             }
         }
         for (int q = 0; q < p.bn && r.violations < 16; ++q) {
-            int px = tr.p0 + q;
-            const bool valid = px <= tr.plast;
-            if (!valid) px = tr.p0;
+            bool valid;
+            const int px = tile_pixel(tr, q, &valid);
             int64_t yoff;
             const int base = cl_pixel_base(cl, tr, a, px, &yoff);
             const int gi = px / (int)g.wo, ii = gi / (int)g.ho;

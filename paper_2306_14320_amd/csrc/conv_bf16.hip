@@ -456,9 +456,7 @@ __global__ __launch_bounds__(kConvThreads) void conv_bf16_kernel(ConvArgs a) {
     bool pvalid[NP];
 #pragma unroll
     for (int pb = 0; pb < NP; ++pb) {
-        int p = tr.p0 + wp_ * TP + pb * 32 + l32;
-        pvalid[pb] = p <= tr.plast;
-        if (!pvalid[pb]) p = tr.p0;
+        const int p = tile_pixel(tr, wp_ * TP + pb * 32 + l32, &pvalid[pb]);
         so[pb] = (kl * a.cl_pb + cl_pixel_base(cl, tr, a, p, &yoff[pb])) * 8;
     }
     int fo[NJ];
@@ -585,9 +583,7 @@ __global__ __launch_bounds__(NT) void conv_bf16_fast_kernel(ConvArgs a) {
     bool pvalid[NP];
 #pragma unroll
     for (int pb = 0; pb < NP; ++pb) {
-        int p = tr.p0 + wp_ * TP + pb * 32 + l32;
-        pvalid[pb] = p <= tr.plast;
-        if (!pvalid[pb]) p = tr.p0;
+        const int p = tile_pixel(tr, wp_ * TP + pb * 32 + l32, &pvalid[pb]);
         so[pb] = (kl * a.cl_pb + cl_pixel_base(cl, tr, a, p, &yoff[pb])) * 8;
     }
     int fo[NJ];
@@ -780,9 +776,7 @@ __global__ __launch_bounds__(NT) void conv_bf16_fused_kernel(ConvArgs a) {
     bool pvalid[NP];
 #pragma unroll
     for (int pb = 0; pb < NP; ++pb) {
-        int p = tr.p0 + wp_ * TP + pb * 32 + l32;
-        pvalid[pb] = p <= tr.plast;
-        if (!pvalid[pb]) p = tr.p0;
+        const int p = tile_pixel(tr, wp_ * TP + pb * 32 + l32, &pvalid[pb]);
         so[pb] = (kl * a.cl_pb + cl_pixel_base(cl, tr, a, p, &yoff[pb])) * 8;
     }
     int fo[NJ];

@@ -82,7 +82,8 @@ struct TileRuns {
 
     __host__ __device__ void init(int ptile, int bn, const ConvArgs& a) {
         p0 = ptile * bn;
-        plast = (p0 + bn < a.npix ? p0 + bn : a.npix) - 1;
+        // (unsigned: p0 + bn may pass 2^31)
+        plast = (int)((uint32_t)p0 + bn < (uint32_t)a.npix ? (uint32_t)p0 + bn : (uint32_t)a.npix) - 1;
         const int g0 = (int)fast_div((uint32_t)p0, a.div_wo);
         const int g1 = (int)fast_div((uint32_t)plast, a.div_wo);
         n0 = p0 - g0 * a.wo;
@@ -150,6 +151,14 @@ __host__ __device__ inline SegRun seg_run(int s, int nseg, int len0, int len_mid
     r.m = s == 0 ? m0 : 0;
     r.q = s == 0 ? qa0 : 0;
     return r;
+}
+
+// Pixel `off` of a tile (0 <= off < bn); one past the tile's last is its first
+// (computed, never stored).  Unsigned: p0 + off may pass 2^31.
+__host__ __device__ inline int tile_pixel(const TileRuns& tr, int off, bool* valid) {
+    const uint32_t p = (uint32_t)tr.p0 + off;
+    *valid = p <= (uint32_t)tr.plast;
+    return *valid ? (int)p : tr.p0;
 }
 
 // Strip offset of the window of pixel p (its column in the implicit GEMM) and

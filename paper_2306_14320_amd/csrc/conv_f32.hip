@@ -744,9 +744,7 @@ __global__ __launch_bounds__(NT) void conv_f32_kernel(ConvArgs a) {
     bool pvalid[NP];
 #pragma unroll
     for (int pb = 0; pb < NP; ++pb) {
-        int p = tr.p0 + wp_ * TP + pb * 32 + l32;
-        pvalid[pb] = p <= tr.plast;
-        if (!pvalid[pb]) p = tr.p0;
+        const int p = tile_pixel(tr, wp_ * TP + pb * 32 + l32, &pvalid[pb]);
         sl[pb] = pixel_base(tr, a, p, &yoff[pb]) + kl * ds;
     }
     int fl[NJ];
